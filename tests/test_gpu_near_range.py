@@ -1,0 +1,57 @@
+"""The near field of mixed plans where pairs, cells or moments differ by many
+powers of two: each dipole's own error against the direct sum.
+
+Bar: 1e-6 of the sum of the contributions' magnitudes, 2 |m_j| / r_ij^3 over the
+sources j of a dipole.  A contribution takes a dozen FP32 roundings, 12 x 2^-24 =
+7e-7 at worst, and the two FP16 numbers that stand for each of its factors add
+2^-24 each; the positions are exact to 2^-48 of a cell side, and the cases are
+small enough for every pair to be in the near field.
+"""
+import numpy as np
+import pytest
+
+from paper_0810_0233_amd import ccfmm, inputs
+
+pytestmark = pytest.mark.gpu
+BAR = 1e-6
+
+
+@pytest.fixture(scope="module")
+def ref():
+    import oracle
+
+    return oracle
+
+
+def run(pos, m, **kw):
+    pl = ccfmm.Plan.create(pos, ccfmm.params(max_batch=m.shape[0], precision=ccfmm.PREC_MIXED, **kw))
+    assert pl.info()["n_m2l_pairs"] == 0  # near field only
+    return pl.eval(m)
+
+
+def worst(ref, H, pos, m):
+    """Largest error of a dipole over the magnitude of its contributions."""
+    r2 = np.zeros((pos.shape[0], pos.shape[0]))
+    for a in range(3):
+        r2 += (pos[:, None, a] - pos[None, :, a]) ** 2
+    inv3 = np.where(r2 > 0, r2, np.inf) ** -1.5
+    S = inv3 @ (2.0 * np.linalg.norm(m, axis=1))
+    err = np.linalg.norm(H - ref.bruteforce(pos, m), axis=1)
+    assert np.isfinite(H).all()
+    return float((err[S > 0] / S[S > 0]).max())
+
+
+# separations down to where 1/r^3 leaves FP32 (positions that FP32 pairs hold exactly)
+@pytest.mark.parametrize("nb", [1, 3, 16, 32])
+@pytest.mark.parametrize("power", [-30, -37, -39, -41])
+def test_smallest_separations(ref, power, nb):
+    rng = np.random.default_rng(10)
+    n = 40
+    a = rng.permutation(np.array(np.meshgrid(*[np.arange(1, 64, 9)] * 3)).reshape(3, -1).T)[:n] / 64.0
+    pos = np.concatenate([a, a + np.array([2.0 ** power, 0.0, 2.0 ** (power - 1)])])
+    m = np.stack([inputs.random_moments(2 * n, 70 + b) for b in range(nb)])
+    H = run(pos, m, order=3, theta=0.5, leaf_target=2.0 * n, box=(np.zeros(3), np.ones(3)))
+    for b in sorted({0, nb - 1}):
+        e = worst(ref, H[b], pos, m[b])
+        print("case power=%d nb=%d b=%d" % (power, nb, b), e, flush=True)
+        assert e <= BAR
