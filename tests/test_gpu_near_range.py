@@ -41,6 +41,28 @@ def worst(ref, H, pos, m):
     return float((err[S > 0] / S[S > 0]).max())
 
 
+# Flat and long cells (a sheet, a rod) and a small opening angle: near cells that
+# lie far away in units of the smallest side.  One configuration holds a single
+# moment.  Outside the adjacent cells a position is rounded in the other cell's
+# frame, at up to twice the separation r: 2^-24 of it in three coordinates and the
+# fourth power of 1/r, 4 sqrt(3) 2^-24 x 2 = 8e-7 more.
+@pytest.mark.parametrize("nb", [3, 16, 32])
+@pytest.mark.parametrize("sides,levels,theta", [((8.0, 8.0, 1e-4), 6, 0.1), ((8.0, 8.0, 0.03), 6, 0.1),
+                                                ((64.0, 0.02, 1.0), 6, 0.02), ((32.0, 32.0, 32.0), 9, 0.08),
+                                                ((128.0, 1.0, 1.0), 7, 0.01)])
+def test_far_near_cells(ref, sides, levels, theta, nb):
+    rng = np.random.default_rng(9)
+    n = 600
+    pos = rng.random((n, 3)) * np.array(sides)
+    m = np.stack([inputs.random_moments(n, 90 + b) for b in range(nb)])
+    m[1, 1:] = 0.0
+    H = run(pos, m, order=2, theta=theta, leaf_target=n / 2.0 ** levels, box=(np.zeros(3), np.array(sides)))
+    for b in (0, 1, nb - 1):
+        e = worst(ref, H[b], pos, m[b])
+        print("case sides=%s nb=%d b=%d" % (sides, nb, b), e, flush=True)
+        assert e <= 2 * BAR
+
+
 # separations down to where 1/r^3 leaves FP32 (positions that FP32 pairs hold exactly)
 @pytest.mark.parametrize("nb", [1, 3, 16, 32])
 @pytest.mark.parametrize("power", [-30, -37, -39, -41])
