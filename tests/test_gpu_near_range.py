@@ -41,6 +41,50 @@ def worst(ref, H, pos, m):
     return float((err[S > 0] / S[S > 0]).max())
 
 
+# A dipole beside a much closer one that has no moment, or next to none: the
+# field is that of the others.  One cell side is 1/2 (8 cells, all of them near).
+@pytest.mark.parametrize("nb", [2, 3, 16, 32])
+@pytest.mark.parametrize("gap", [1e-1, 1e-2, 1e-3, 1e-4, 1e-6, 1e-7])
+def test_close_partner_without_moment(ref, gap, nb):
+    rng = np.random.default_rng(7)
+    n = 150
+    a = rng.random((n, 3))
+    d = rng.standard_normal((n, 3))
+    pos = np.concatenate([a, a + 0.5 * gap * d / np.linalg.norm(d, axis=1)[:, None]]).clip(0, 1)
+    m = np.stack([inputs.random_moments(2 * n, 30 + b) for b in range(nb)])
+    m[0, n:] = 0.0
+    m[1, n:] *= 1e-9
+    if nb > 2:
+        m[nb - 1, n:] *= np.exp2(-rng.integers(0, 20, n))[:, None]
+    H = run(pos, m, order=3, theta=0.5, leaf_target=2 * n / 8.0, box=(np.zeros(3), np.ones(3)))
+    for b in sorted({0, 1, nb - 1}):
+        e = worst(ref, H[b], pos, m[b])
+        print("case gap=%g nb=%d b=%d" % (gap, nb, b), e, flush=True)
+        assert e <= BAR
+
+
+# gaps of every size at once: several separate ranges of 1/r^3 in one step
+@pytest.mark.parametrize("nb", [3, 16, 32])
+def test_gaps_of_every_size(ref, nb):
+    rng = np.random.default_rng(8)
+    gap = np.repeat(10.0 ** -np.arange(0.5, 7.0, 0.25), 6)
+    n = gap.size
+    centre = rng.random((6, 3)) * 0.8 + 0.1
+    d = rng.standard_normal((n, 3))
+    pos = centre[np.arange(n) % 6] + gap[:, None] * d / np.linalg.norm(d, axis=1)[:, None]
+    pos = np.concatenate([pos, centre]).clip(0, 1)
+    n = pos.shape[0]
+    m = np.stack([inputs.random_moments(n, 60 + b) for b in range(nb)])
+    r = np.concatenate([gap, np.full(6, 1e-7)])
+    m[0, r < 1e-2] = 0.0
+    m[1, r < 1e-4] = 0.0
+    H = run(pos, m, order=3, theta=0.5, leaf_target=n / 2.0, box=(np.zeros(3), np.ones(3)))
+    for b in (0, 1, nb - 1):
+        e = worst(ref, H[b], pos, m[b])
+        print("case nb=%d b=%d" % (nb, b), e, flush=True)
+        assert e <= BAR
+
+
 # Flat and long cells (a sheet, a rod) and a small opening angle: near cells that
 # lie far away in units of the smallest side.  One configuration holds a single
 # moment.  Outside the adjacent cells a position is rounded in the other cell's
