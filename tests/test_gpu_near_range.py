@@ -121,3 +121,22 @@ def test_smallest_separations(ref, power, nb):
         e = worst(ref, H[b], pos, m[b])
         print("case power=%d nb=%d b=%d" % (power, nb, b), e, flush=True)
         assert e <= BAR
+
+
+# A batch is as accurate as its configurations are alone, where the near field runs
+# on the FP32 vector units: rms of each dipole's error against the FP64 plan.
+@pytest.mark.parametrize("order,nb", [(3, 3), (4, 8), (5, 16), (4, 32)])
+def test_batch_as_accurate_as_one(order, nb):
+    pos, box = inputs.ferrofluid(20000, order)
+    m = np.stack([inputs.random_moments(20000, b) for b in range(nb)])
+
+    def field(m, precision):
+        kw = dict(order=order, theta=0.5, box=box, max_batch=m.shape[0])
+        return ccfmm.Plan.create(pos, ccfmm.params(precision=precision, **kw)).eval(m)
+
+    D = field(m[:3], ccfmm.PREC_FP64)
+    batch = field(m, ccfmm.PREC_MIXED)[:3]
+    one = np.stack([field(m[b:b + 1], ccfmm.PREC_MIXED)[0] for b in range(3)])
+    e, e1 = (float(np.sqrt(np.mean(np.sum((H - D) ** 2, -1) / np.sum(D ** 2, -1)))) for H in (batch, one))
+    print("case order=%d nb=%d" % (order, nb), e, e1, flush=True)
+    assert e <= e1
