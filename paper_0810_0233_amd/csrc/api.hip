@@ -248,7 +248,7 @@ static void size_expansions(Plan& P, int nb) {
   // (else the near field runs on the vector units)
   const bool f16 = P.has_gran && near_f16_wanted(P, nb) && spare_room(P, [&] {
                      P.gran_m.ensure(near_f16_moment_bytes(P, nb));
-                     P.gran_top.ensure(sizeof(uint32_t) * nb);
+                     P.gran_top.ensure(sizeof(uint32_t) * 2 * nb);
                    });
   for (int l = 0; l <= P.L; l++) P.lev[l]->qoff = qoff[l];
   P.near_f16 = f16;

@@ -47,6 +47,8 @@ struct P2PArgs {
   const int32_t* leaf_p;     // per-cell local order (compact leaves), or null
   const float* yhi;          // FP32 positions (SoA [3][n])
   const float* ylo;          // FP32 residuals of the positions (SoA [3][n]); null in FP64
+  const uint32_t* range;     // null, or (k_p2p_multi) the moments' ranges: only configurations
+                             // that the FP16 form leaves (moments_wide) are computed
 };
 
 // readlane of a float or double held as bits
@@ -74,6 +76,14 @@ __device__ __forceinline__ int64_t xcd_run_block(int nblk, int bid) {
   if (bid >= full) return bid;
   const int x = bid & 7, s = bid >> 3;
   return ((int64_t)(s / kXcdRun) * 8 + x) * kXcdRun + s % kXcdRun;
+}
+
+// Whether configuration b's moments are too far apart for the FP16 near field, or
+// not finite.  range: FP32 bits of the largest one, and of the smallest less one,
+// of nb configurations each.
+__device__ __forceinline__ bool moments_wide(const uint32_t* range, int nb, int b) {
+  const uint32_t top = range[b], low = range[nb + b];  // (low: all ones without any moment)
+  return top >= 0x7f800000u || (low != 0xffffffffu && (int)(top >> 23) - (int)((low + 1) >> 23) > 27);
 }
 
 P2PArgs p2p_args(Plan& P, int nb, bool fp64);

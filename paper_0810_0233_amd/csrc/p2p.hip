@@ -580,6 +580,14 @@ __global__ void __launch_bounds__(64 * kP2PWaves, (multi_waves<T, KB, PL>())) k_
   if (!kSplit && !live) return;
   const int cfg0 = a.cfg0 + blockIdx.y * KB;
   const int ncfg = min(KB, a.nb - cfg0);  // configurations of this group inside the batch
+  uint32_t wanted = ~0u;
+  if constexpr (std::is_same<T, float>::value && PL == 0) {
+    if (a.range) {
+      wanted = 0;
+      for (int b = 0; b < ncfg; b++) wanted |= (uint32_t)moments_wide(a.range, a.nb, cfg0 + b) << b;
+      if (wanted == 0) return;
+    }
+  }
   const P2PChunk ch = a.chunks[live ? si.item : 0];
   const int n = (int)a.n;
   const int c = ch.count;
@@ -785,7 +793,7 @@ __global__ void __launch_bounds__(64 * kP2PWaves, (multi_waves<T, KB, PL>())) k_
       (void)V;
 #pragma unroll
       for (int b = 0; b < KB; b++) {
-        if (b < ncfg) {
+        if (b < ncfg && (wanted >> b & 1)) {
           double* o = H + ((int64_t)(cfg0 + b) * n + pi) * 3;
           o[0] = s3 * h[b][0];
           o[1] = s3 * h[b][1];
@@ -905,6 +913,7 @@ P2PArgs p2p_args(Plan& P, int nb, bool fp64) {
   a.leaf_p = P.has_leaf ? P.leaf_p.as<int32_t>() : nullptr;
   a.yhi = P.yf.as<float>();
   a.ylo = fp64 ? nullptr : P.yf.as<float>() + 3 * P.n;
+  a.range = nullptr;
   return a;
 }
 
@@ -1024,6 +1033,9 @@ static void near_impl(Plan& P, int nb, double* d_H, hipStream_t st) {
   P2PArgs a = p2p_args(P, nb, fp64);
   if (nb >= 2 && !fp64 && P.near_f16) {
     run_near_f16(P, nb, d_H, st);
+    CCFMM_HIP(hipGetLastError());
+    a.range = P.gran_top.as<uint32_t>();
+    multi_dispatch<T, 0>(P, a, y, nb, d_H, st);
   } else if (nb >= 2) {
     multi_dispatch<T, 0>(P, a, y, nb, d_H, st);
   } else {

@@ -121,7 +121,7 @@ struct Plan {
   int64_t nchunks_b_cap = 0;  // capacity of that list (the launches cover it)
   // FP16 near field of a mixed plan: granules of 8 sources (first of each cell,
   // first dipole and count of each), their positions and residuals, and the
-  // split moments of an evaluation with each configuration's largest component
+  // split moments of an evaluation with each configuration's largest and smallest
   DevBuf gran_start, gran_src, gran_pos, gran_m, gran_top;
   int64_t ngran_cap = 0;
   bool has_gran = false;   // granules are laid out for the current positions

@@ -78,8 +78,9 @@ def test_gaps_of_every_size(ref, nb):
     r = np.concatenate([gap, np.full(6, 1e-7)])
     m[0, r < 1e-2] = 0.0
     m[1, r < 1e-4] = 0.0
+    m[2] *= (r ** 3)[:, None]  # every shell gives the centre the same
     H = run(pos, m, order=3, theta=0.5, leaf_target=n / 2.0, box=(np.zeros(3), np.ones(3)))
-    for b in (0, 1, nb - 1):
+    for b in sorted({0, 1, 2, nb - 1}):
         e = worst(ref, H[b], pos, m[b])
         print("case nb=%d b=%d" % (nb, b), e, flush=True)
         assert e <= BAR
@@ -121,6 +122,30 @@ def test_smallest_separations(ref, power, nb):
         e = worst(ref, H[b], pos, m[b])
         print("case power=%d nb=%d b=%d" % (power, nb, b), e, flush=True)
         assert e <= BAR
+
+
+# Moments of very different size, the small ones in close pairs whose field is
+# their own, and two configurations without such a spread beside them.
+@pytest.mark.parametrize("nb", [3, 12, 16, 40])
+@pytest.mark.parametrize("power", [-27, -29, -45, -60])
+def test_moment_spread(ref, power, nb):
+    rng = np.random.default_rng(11)
+    n = 100
+    gap = 0.3 * 2.0 ** (power / 3.0)
+    a = rng.random((n, 3)) * np.array([0.5, 1.0, 1.0])
+    d = rng.standard_normal((n, 3))
+    pos = np.concatenate([a, a + 0.5 * gap * d / np.linalg.norm(d, axis=1)[:, None], [[0.99, 0.5, 0.5]]]).clip(0, 1)
+    m = np.stack([inputs.random_moments(2 * n + 1, 40 + b) for b in range(nb)])
+    for b in (0, nb // 2):
+        m[b, :-1] *= 2.0 ** power
+    H = run(pos, m, order=3, theta=0.5, leaf_target=(2 * n + 1) / 8.0, box=(np.zeros(3), np.ones(3)))
+    for b in (0, nb // 2, nb - 1):
+        e = worst(ref, H[b], pos, m[b])
+        print("case power=%d nb=%d b=%d" % (power, nb, b), e, flush=True)
+        assert e <= BAR
+    H2 = run(pos, np.delete(m, [0, nb // 2], axis=0) if nb > 4 else m[1:], order=3, theta=0.5,
+             leaf_target=(2 * n + 1) / 8.0, box=(np.zeros(3), np.ones(3)))
+    assert np.abs(H2[-1] - H[-1]).max() <= BAR * np.abs(H[-1]).max()
 
 
 # A batch is as accurate as its configurations are alone, where the near field runs
