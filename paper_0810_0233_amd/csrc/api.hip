@@ -724,7 +724,7 @@ static int create_common(ccfmm_plan* out, int64_t n, const double* d_pos, const 
     ccfmm_plan pl = new ccfmm_plan_s();
     Plan& P = pl->P;
     P.mem.cap = prm->device_mem_cap;
-    P.mem.spare = [](void* p) { return static_cast<Plan*>(p)->drop_granules(); };
+    P.mem.spare = [](void* p) { return static_cast<Plan*>(p)->give_back(); };
     P.mem.owner = &P;
     try {
       BudgetScope bs(&P.mem);

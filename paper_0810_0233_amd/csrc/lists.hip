@@ -641,7 +641,8 @@ __global__ void k_tile_keys(int64_t ntiles, const M2LTile* tiles, uint32_t* key,
 constexpr int64_t kM2LSplitBelow = 512, kM2LSplitBlocks = 1024;
 constexpr int kM2LPartSteps = 12;
 
-void build_m2l_tiles(Plan& P, int nbatch, hipStream_t st) {
+// may_split: step lists of a small system may be cut into parts
+static void tile_targets(Plan& P, int nbatch, bool may_split, hipStream_t st) {
   const int L = P.L;
   const int T = 256;
   const int cols = m2l_tile_cols(P.m2l_variant);
@@ -721,32 +722,37 @@ void build_m2l_tiles(Plan& P, int nbatch, hipStream_t st) {
   // with fewer blocks than compute units takes the time of its longest list:
   // the lists are cut (traceless wide kernels; the parts' sums are added by
   // k_m2l_sum in part order).
-  P.m2l_split = red && ntiles < kM2LSplitBelow && nsteps * P.ncg > ntiles * kM2LPartSteps;
+  // What whole lists need comes first: the parts' sums and their longer tile lists
+  // are taken where there is room beside it.
+  int32_t* step_delta = reinterpret_cast<int32_t*>(P.step_delta.ensure(sizeof(int32_t) * std::max<int64_t>(1, nsteps)));
+  int32_t* step_src = reinterpret_cast<int32_t*>(P.step_src.ensure(sizeof(int32_t) * std::max<int64_t>(1, nsteps * TC)));
+  int32_t* tile_tgt = reinterpret_cast<int32_t*>(P.tile_tgt.ensure(sizeof(int32_t) * std::max<int64_t>(1, ngroups * TC)));
+  P.tiles.ensure(sizeof(M2LTile) * std::max<int64_t>(1, ntiles));
+  P.tile_order.ensure(sizeof(int32_t) * 4 * std::max<int64_t>(1, ntiles));
+  P.m2l_split = may_split && red && ntiles < kM2LSplitBelow && nsteps * P.ncg > ntiles * kM2LPartSteps;
   P.nlaunch = ntiles;
   int32_t* poff = nullptr;
   const int most = (int)std::max<int64_t>(kM2LPartSteps, (nsteps * P.ncg + kM2LSplitBlocks - 1) / kM2LSplitBlocks);
+  const int64_t nparts = P.ncg * (ngroups + nsteps / most);  // at least the sum of max(1, ceil(count / most))
   if (P.m2l_split) {
-    const int64_t nparts = P.ncg * (ngroups + nsteps / most);  // at least the sum of max(1, ceil(count / most))
     const size_t es = P.precision == CCFMM_PREC_FP64 ? sizeof(double) : sizeof(float);
-    try {
+    P.m2l_split = optional_room(P, [&] {
       P.m2l_part.ensure(es * (size_t)nparts * cols * nred_stride(P.p));
-      P.nlaunch = nparts;
-    } catch (const StatusError& e) {
-      if (e.status != CCFMM_ENOMEM) throw;
-      P.m2l_split = false;  // no room under the plan's cap for the parts' sums: whole lists
-    }
+      P.part_off.ensure(sizeof(int32_t) * 2 * (ngroups + 1));
+      P.tiles.ensure(sizeof(M2LTile) * nparts);
+      P.tile_order.ensure(sizeof(int32_t) * 4 * nparts);
+    });
+    if (!P.m2l_split) P.m2l_part.release();
   }
   if (P.m2l_split) {
-    int32_t* pb = reinterpret_cast<int32_t*>(P.part_off.ensure(sizeof(int32_t) * 2 * (ngroups + 1)));
+    P.nlaunch = nparts;
+    int32_t* pb = P.part_off.as<int32_t>();
     poff = pb + ngroups + 1;
     k_part_count<<<ceil_div(ngroups, T), T, 0, st>>>(ngroups, gcnt, most, pb);
     CCFMM_HIP(hipGetLastError());
     scan_exclusive(pb, poff, ngroups, P.scratch, st);
   }
-  int32_t* step_delta = reinterpret_cast<int32_t*>(P.step_delta.ensure(sizeof(int32_t) * std::max<int64_t>(1, nsteps)));
-  int32_t* step_src = reinterpret_cast<int32_t*>(P.step_src.ensure(sizeof(int32_t) * std::max<int64_t>(1, nsteps * TC)));
-  int32_t* tile_tgt = reinterpret_cast<int32_t*>(P.tile_tgt.ensure(sizeof(int32_t) * std::max<int64_t>(1, ngroups * TC)));
-  M2LTile* tiles = reinterpret_cast<M2LTile*>(P.tiles.ensure(sizeof(M2LTile) * std::max<int64_t>(1, P.nlaunch)));
+  M2LTile* tiles = P.tiles.as<M2LTile>();
   k_group_steps<<<ceil_div(ngroups, 4), T, 0, st>>>(TL, ngroups, bitmap, wpre, goff, step_delta);
   CCFMM_HIP(hipGetLastError());
   if (ngroups > 0) {
@@ -767,13 +773,24 @@ void build_m2l_tiles(Plan& P, int nbatch, hipStream_t st) {
   // launch order: longest step lists first, so the dispatcher's greedy,
   // round-robin placement balances the XCDs and their compute units
   if (P.nlaunch > 0) {
-    int32_t* ord = reinterpret_cast<int32_t*>(P.tile_order.ensure(sizeof(int32_t) * 4 * P.nlaunch));
+    int32_t* ord = P.tile_order.as<int32_t>();
     uint32_t* key = reinterpret_cast<uint32_t*>(ord + P.nlaunch);
     int32_t* ord2 = ord + 2 * P.nlaunch;
     uint32_t* key2 = reinterpret_cast<uint32_t*>(ord + 3 * P.nlaunch);
     k_tile_keys<<<ceil_div(P.nlaunch, T), T, 0, st>>>(P.nlaunch, tiles, key, ord);
     CCFMM_HIP(hipGetLastError());
     radix_sort_pairs(key, ord, key2, ord2, P.nlaunch, 16, P.scratch, st);
+  }
+}
+
+void build_m2l_tiles(Plan& P, int nbatch, hipStream_t st) {
+  try {
+    tile_targets(P, nbatch, true, st);
+  } catch (const StatusError& e) {
+    // the parts' sums, of these lists or of an earlier batch, took the room
+    if (e.status != CCFMM_ENOMEM || !P.m2l_part.p) throw;
+    P.m2l_part.release();
+    tile_targets(P, nbatch, false, st);
   }
 }
 

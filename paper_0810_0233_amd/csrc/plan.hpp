@@ -168,6 +168,14 @@ struct Plan {
     qv_batch = 0;
     return true;
   }
+  // (MemBudget::spare)
+  bool give_back() {
+    if (m2l_part.p && !m2l_split) {  // of an earlier batch's tiles
+      m2l_part.release();
+      return true;
+    }
+    return drop_granules();
+  }
   ~Plan() {
     drop_graph();
     if (ev_fork) (void)hipEventDestroy(ev_fork);
@@ -188,25 +196,40 @@ void build_p2p_chunks(Plan& P, hipStream_t st);
 // whether a mixed plan's near field of nb configurations runs on the FP16 matrix
 // cores, which take the same time for 1 to 8
 bool near_f16_wanted(const Plan& P, int nb);
-// alloc(), buffers the plan can do without; false where its cap has no room
+// alloc(), buffers the plan can do without: nothing is given back for them, nor do
+// they take the room of the positions that are still to come in (a plan with bf16
+// operators gives those up for the positions).  False where the cap has no room;
+// what was allocated until then is kept.
 template <typename F>
-bool spare_room(Plan& P, F&& alloc) {
-  const auto spare = P.mem.spare;
-  P.mem.spare = nullptr;  // nothing is given back for these
-  bool ok = true;
+bool optional_room(Plan& P, F&& alloc) {
+  struct Scope {
+    Plan& P;
+    decltype(P.mem.spare) spare;
+    int64_t later;
+    explicit Scope(Plan& q) : P(q), spare(q.mem.spare), later(q.ops_bf16 ? 0 : q.pos_later) {
+      P.mem.spare = nullptr;
+      P.mem.used += later;
+    }
+    ~Scope() {
+      P.mem.spare = spare;
+      P.mem.used -= later;
+    }
+  } scope(P);
   try {
     alloc();
   } catch (const StatusError& e) {
-    P.mem.spare = spare;
     if (e.status != CCFMM_ENOMEM) throw;
-    ok = false;
-  } catch (...) {
-    P.mem.spare = spare;
-    throw;
+    return false;
   }
-  P.mem.spare = spare;
-  if (!ok) P.has_gran = true, P.drop_granules();
-  return ok;
+  return true;
+}
+// the same for the FP16 near field's buffers, all of them given back if one has no room
+template <typename F>
+bool spare_room(Plan& P, F&& alloc) {
+  if (optional_room(P, alloc)) return true;
+  P.has_gran = true;
+  P.drop_granules();
+  return false;
 }
 void build_granules(Plan& P, hipStream_t st);
 size_t near_f16_moment_bytes(const Plan& P, int nb);

@@ -122,3 +122,27 @@ def test_m2l_parts_match_oracle(ref, order, variant):
     H2, pl2 = eval_on_stream(pos, m, order=order, theta=0.5, leaf_target=4, box=box, m2l_variant=ccfmm.M2L_BLOCK)
     assert rel_rms(H, H2) <= 1e-12
     assert cap > 0
+
+
+# a plan with no room for the parts' sums keeps its lists whole: nothing else goes
+# for them (neither the plan itself nor the FP16 near field's buffers, which the
+# evaluation would miss), and the field is the same
+@pytest.mark.parametrize("precision,bar", [(ccfmm.PREC_FP64, 1e-12), (ccfmm.PREC_MIXED, 1e-6)])
+@pytest.mark.parametrize("order,nb", [(5, 1), (5, 3), (4, 3)])
+def test_cap_without_room_for_parts(order, nb, precision, bar):
+    pos, box = inputs.lattice(14, 11, 9)
+    m = np.stack([inputs.random_moments(pos.shape[0], 20 + b) for b in range(nb)])
+    kw = dict(order=order, theta=0.5, leaf_target=4, box=box, precision=precision, max_batch=nb)
+    pl = ccfmm.Plan.create(pos, ccfmm.params(**kw))
+    made = pl.info()["device_bytes"]
+    H = pl.eval(m)
+    held = pl.info()["device_bytes"] - made  # what an evaluation adds
+    whole = ccfmm.Plan.create(pos, ccfmm.params(device_mem_cap=made - 1, **kw)).info()["device_bytes"]
+    assert held < made - whole
+    for cap in (made - 1, whole + held):
+        print("case order=%d nb=%d precision=%d cap=%d of %d" % (order, nb, precision, cap, made), flush=True)
+        pl2 = ccfmm.Plan.create(pos, ccfmm.params(device_mem_cap=cap, **kw))
+        made2 = pl2.info()["device_bytes"]
+        assert made2 <= whole
+        assert rel_rms(pl2.eval(m), H) <= bar
+        assert pl2.info()["device_bytes"] - made2 == held
