@@ -492,6 +492,7 @@ static void build_all(Plan& P, const double* d_pos, hipStream_t st, bool was_bui
     P.ops_bf16 = false;
     P.Dx.release();
     P.dtab_p = 0;
+    P.gran_off = false;
     build_dtensors(P, st);
     rest();
   }

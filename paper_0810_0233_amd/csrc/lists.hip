@@ -898,7 +898,7 @@ void build_p2p_chunks(Plan& P, hipStream_t st) {
   };
   if (fp64) {
     if (P.nbmax >= 2) pieces();
-  } else if (near_f16_wanted(P, P.nbmax)) {
+  } else if (near_f16_wanted(P, P.nbmax) && !P.gran_off) {
     P.has_gran = false;
     P.has_gran = spare_room(P, [&] {
       pieces();

@@ -125,6 +125,7 @@ struct Plan {
   DevBuf gran_start, gran_src, gran_pos, gran_m, gran_top;
   int64_t ngran_cap = 0;
   bool has_gran = false;   // granules are laid out for the current positions
+  bool gran_off = false;   // they were given back once: not laid out again for later positions
   bool near_f16 = false;  // the current batch runs that near field
   DevBuf scratch;    // scan/sort temporaries
   DevBuf scratch2;
@@ -165,6 +166,7 @@ struct Plan {
     drop_graph();
     for (DevBuf* b : {&gran_start, &gran_src, &gran_pos, &gran_m, &gran_top, &chunks_b}) b->release();
     has_gran = near_f16 = false;
+    gran_off = true;
     qv_batch = 0;
     return true;
   }

@@ -133,3 +133,31 @@ def test_memory_cap_falls_back(nb):
         pl2.update_positions_device(d_pos2.data_ptr())
         H3, _ = run(pos2, m, **kw)
         assert rel_rms(pl2.eval(m), H3) <= BAR
+
+
+# a plan that gave the near field's buffers back does not fill and hold them again
+# for positions that keep its cells, nor for others
+@pytest.mark.parametrize("nb", [3, 40])
+def test_given_back_stays_given_back(nb):
+    import torch
+
+    rng = np.random.default_rng(7)
+    pos = rng.random((6000, 3))
+    m = np.stack([inputs.random_moments(6000, 5 + b) for b in range(nb)])
+    kw = dict(order=3, theta=0.5, leaf_target=12.0, box=(np.zeros(3), np.ones(3)))
+    H, pl = run(pos, m, **kw)
+    need = pl.info()["device_bytes"]
+    split = 768 * ((nb + 7) // 8) * (6000 // 8)
+    H2, pl2 = run(pos, m, device_mem_cap=need - split, **kw)
+    held = pl2.info()["device_bytes"]
+    assert held < need - split
+    for k, p in enumerate((pos, pos + 1e-9, (0.5 * pos).clip(0, 1), pos)):
+        kept = pl2.info()["n_rebuilds_kept"]
+        d = torch.from_numpy(np.ascontiguousarray(p.clip(0, 1))).cuda()
+        torch.cuda.synchronize()
+        pl2.update_positions_device(d.data_ptr())
+        assert (pl2.info()["n_rebuilds_kept"] > kept) == (k < 2)
+        assert pl2.info()["device_bytes"] <= held + (0 if k < 2 else split // 2)
+        G, _ = run(p.clip(0, 1), m, **kw)
+        assert rel_rms(pl2.eval(m), G) <= BAR
+        print("case nb=%d update %d: %d of %d bytes" % (nb, k, pl2.info()["device_bytes"], held), flush=True)
