@@ -28,7 +28,9 @@ void* DevBuf::ensure(size_t bytes) {
   MemBudget* b = current_budget();
   if (b && b->cap > 0) {
     auto fits = [&] { return b->used - (budget == b ? (int64_t)cap : 0) + (int64_t)bytes <= b->cap; };
-    if (!fits() && !(b->spare && b->spare(b->owner) && fits()))
+    while (!fits() && b->spare && b->spare(b->owner, false)) {
+    }
+    if (!fits())
       throw StatusError{CCFMM_ENOMEM, "plan device-memory cap of " + std::to_string(b->cap) + " bytes: holding " +
                                           std::to_string(b->used) + ", a buffer of " + std::to_string(bytes) +
                                           " bytes does not fit"};
@@ -37,6 +39,10 @@ void* DevBuf::ensure(size_t bytes) {
   g_devbuf_allocs.fetch_add(1);
   void* q = nullptr;
   hipError_t e = hipMalloc(&q, bytes);
+  while ((e != hipSuccess || q == nullptr) && b && b->spare && b->spare(b->owner, true)) {
+    (void)hipGetLastError();
+    e = hipMalloc(&q, bytes);
+  }
   if (e != hipSuccess || q == nullptr) {
     (void)hipGetLastError();
     throw StatusError{CCFMM_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed"};
@@ -520,17 +526,27 @@ static void prepare_batch(Plan& P, int nb, hipStream_t st) {
 static void prepare_batch_impl(Plan& P, int nb, hipStream_t st) {
   if (nb < 1 || nb > P.nbmax) fail(CCFMM_EINVAL, "nbatch must be in 1..max_batch");
   const int tb = tile_batch(nb, m2l_tile_cols(P.m2l_variant));
-  if (tb != P.TB || ceil_div(nb, tb) != P.ncg || P.tiles_variant != P.m2l_variant ||
-      P.tiles_class_bits != P.class_bits) {
-    P.drop_graph();
-    build_m2l_tiles(P, nb, st);
-    P.info.n_m2l_tiles = P.ntiles;
-    P.info.n_m2l_steps = P.nsteps;
+  // (again where an allocation made the plan give back what was laid out before it,
+  // which happens at most once for each of the three)
+  for (int pass = 0; pass < 4; pass++) {
+    if (P.dtab_p != P.p) {
+      P.drop_graph();
+      build_dtensors(P, st);
+    }
+    if (tb != P.TB || ceil_div(nb, tb) != P.ncg || P.tiles_variant != P.m2l_variant ||
+        P.tiles_class_bits != P.class_bits) {
+      P.drop_graph();
+      build_m2l_tiles(P, nb, st);
+      P.info.n_m2l_tiles = P.ntiles;
+      P.info.n_m2l_steps = P.nsteps;
+    }
+    if (P.qv_batch != nb) {
+      P.drop_graph();
+      size_expansions(P, nb);
+    }
+    if (P.dtab_p == P.p && P.tiles_variant == P.m2l_variant && P.qv_batch == nb) return;
   }
-  if (P.qv_batch != nb) {
-    P.drop_graph();
-    size_expansions(P, nb);
-  }
+  fail(CCFMM_ENOMEM, "no device memory left for the batch");
 }
 
 static void eval_passes(Plan& P, int nb, const double* d_m, double* d_H, hipStream_t st, hipEvent_t* ev,
@@ -725,7 +741,7 @@ static int create_common(ccfmm_plan* out, int64_t n, const double* d_pos, const 
     ccfmm_plan pl = new ccfmm_plan_s();
     Plan& P = pl->P;
     P.mem.cap = prm->device_mem_cap;
-    P.mem.spare = [](void* p) { return static_cast<Plan*>(p)->give_back(); };
+    P.mem.spare = [](void* p, bool no_memory) { return static_cast<Plan*>(p)->give_back(no_memory); };
     P.mem.owner = &P;
     try {
       BudgetScope bs(&P.mem);
@@ -1203,8 +1219,8 @@ static void refresh_pair_count(Plan& P) {
 static double measure_cost_far(Plan& P, int nb, const double* d_m, hipStream_t st) {
   if (P.has_leaf) apply_leaf_params(P, nullptr, nullptr, st);
   refresh_pair_count(P);
-  prepare_batch(P, nb, st);
   double* Hs = reinterpret_cast<double*>(P.judge_a.ensure(sizeof(double) * 3 * (size_t)P.n * nb));
+  prepare_batch(P, nb, st);
   hipEvent_t ev[9];
   create_pass_events(ev, 9, 5);
   const bool overlap = P.overlap;

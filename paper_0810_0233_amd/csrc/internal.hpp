@@ -171,8 +171,10 @@ struct MemBudget {
   int64_t cap = 0;   // 0: no cap
   int64_t used = 0;
   // gives back buffers the owner can do without (false: none left); called
-  // when an allocation would pass the cap
-  bool (*spare)(void* owner) = nullptr;
+  // when an allocation would pass the cap, or (no_memory) when the device has no
+  // more.  What went is laid out anew before the next evaluation, so no buffer is
+  // allocated between that and its kernels.
+  bool (*spare)(void* owner, bool no_memory) = nullptr;
   void* owner = nullptr;
 };
 MemBudget*& current_budget();  // per thread; null outside plan calls

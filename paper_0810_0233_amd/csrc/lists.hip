@@ -729,7 +729,7 @@ static void tile_targets(Plan& P, int nbatch, bool may_split, hipStream_t st) {
   int32_t* tile_tgt = reinterpret_cast<int32_t*>(P.tile_tgt.ensure(sizeof(int32_t) * std::max<int64_t>(1, ngroups * TC)));
   P.tiles.ensure(sizeof(M2LTile) * std::max<int64_t>(1, ntiles));
   P.tile_order.ensure(sizeof(int32_t) * 4 * std::max<int64_t>(1, ntiles));
-  P.m2l_split = may_split && red && ntiles < kM2LSplitBelow && nsteps * P.ncg > ntiles * kM2LPartSteps;
+  P.m2l_split = may_split && !P.m2l_whole && red && ntiles < kM2LSplitBelow && nsteps * P.ncg > ntiles * kM2LPartSteps;
   P.nlaunch = ntiles;
   int32_t* poff = nullptr;
   const int most = (int)std::max<int64_t>(kM2LPartSteps, (nsteps * P.ncg + kM2LSplitBlocks - 1) / kM2LSplitBlocks);

@@ -107,6 +107,7 @@ struct Plan {
   // of its own that leaves its sums in m2l_part (nlaunch blocks in all)
   int64_t nlaunch = 0;
   bool m2l_split = false;
+  bool m2l_whole = false;  // never again: the parts' sums were given back
   DevBuf part_off, m2l_part;
   // P2P chunks (built on the device; their count stays in device memory)
   DevBuf chunks, chunk_cnt;
@@ -170,13 +171,31 @@ struct Plan {
     qv_batch = 0;
     return true;
   }
-  // (MemBudget::spare)
-  bool give_back() {
+  // (MemBudget::spare)  A cap is kept with what the chosen forms need, except for
+  // the FP16 near field; where the device itself has no more memory, the plan goes
+  // on with the forms that need the least.
+  bool give_back(bool no_memory) {
     if (m2l_part.p && !m2l_split) {  // of an earlier batch's tiles
       m2l_part.release();
       return true;
     }
-    return drop_granules();
+    if (drop_granules()) return true;
+    if (!no_memory) return false;
+    if (m2l_part.p) {
+      drop_graph();
+      m2l_part.release();
+      m2l_whole = true;
+      tiles_variant = -1;
+      return true;
+    }
+    if (ops_bf16 && Dx.p) {
+      drop_graph();
+      Dx.release();
+      ops_bf16 = false;
+      dtab_p = 0;
+      return true;
+    }
+    return false;
   }
   ~Plan() {
     drop_graph();

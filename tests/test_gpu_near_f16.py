@@ -161,3 +161,37 @@ def test_given_back_stays_given_back(nb):
         G, _ = run(p.clip(0, 1), m, **kw)
         assert rel_rms(pl2.eval(m), G) <= BAR
         print("case nb=%d update %d: %d of %d bytes" % (nb, k, pl2.info()["device_bytes"], held), flush=True)
+
+
+def test_device_without_memory_gives_back():
+    """The host-pointer evaluation of a plan for 4,096 configurations of 3.6 million
+    dipoles needs more memory than the GPU has: it fails, the plan has given back
+    what its forms can do without (the FP16 near field's buffers, the bf16 M2L
+    operators, the sums of M2L parts), and evaluates smaller batches without them."""
+    import torch
+
+    n, nb = 3600000, 3
+    rng = np.random.default_rng(8)
+    pos = rng.random((n, 3))
+    m = np.stack([inputs.random_moments(n, b) for b in range(nb)])
+    prm = ccfmm.params(order=6, theta=0.8, leaf_target=1500.0, box=(np.zeros(3), np.ones(3)), max_batch=4096,
+                       precision=ccfmm.PREC_MIXED)
+    pl = ccfmm.Plan.create(pos, prm)
+    d_m = torch.from_numpy(m).cuda()
+    fields = []
+    held = []
+    for k in range(2):
+        d_H = torch.empty_like(d_m)
+        torch.cuda.synchronize()
+        pl.eval_device(nb, d_m.data_ptr(), d_H.data_ptr())
+        torch.cuda.synchronize()
+        fields.append(d_H)
+        held.append(pl.info()["device_bytes"])
+        print("case evaluation %d: %d bytes" % (k, held[k]), flush=True)
+        if k == 0:
+            with pytest.raises(ccfmm.CCFMMError) as e:
+                pl.eval(m)
+            assert e.value.status == ccfmm.ENOMEM
+    assert held[1] <= held[0] - 40 * n
+    d = fields[0] - fields[1]
+    assert float((d * d).sum() / (fields[0] * fields[0]).sum()) <= BAR ** 2
