@@ -53,6 +53,32 @@ def test_direct_targets_block_edges(ref, n, nt):
     assert rel_rms(H[:nt][good], R) <= 1e-12
 
 
+# a dipole so far away that its squared distance leaves FP64 adds nothing, as by the
+# definition (1 / r^3 is zero); one whose place is no number makes no number
+@pytest.mark.parametrize("nt", [1, 300, 1100])
+@pytest.mark.parametrize("place,ok", [(1e200, True), (-1e155, True), (1e140, True), (np.nan, False), (np.inf, False)])
+def test_direct_targets_far_away(ref, place, ok, nt):
+    import torch
+
+    rng = np.random.default_rng(nt)
+    n = 1500
+    pos = rng.random((n, 3)) * 10.0
+    pos[n - 1, 1] = place
+    m = inputs.random_moments(n, nt)
+    idx = rng.integers(0, n - 1, nt).astype(np.int64)
+    d_pos, d_m, d_idx = (torch.from_numpy(v).cuda() for v in (pos, m, idx))
+    d_H = torch.zeros((nt, 3), dtype=torch.float64, device="cuda")
+    print("case place=%g nt=%d" % (place, nt), flush=True)
+    ccfmm.direct_targets_device(n, d_pos.data_ptr(), d_m.data_ptr(), nt, d_idx.data_ptr(), d_H.data_ptr(),
+                                torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    H = d_H.cpu().numpy()
+    if ok:
+        assert rel_rms(H, ref.bruteforce_targets(pos[:n - 1], m[:n - 1], idx)) <= 1e-12
+    else:
+        assert np.isnan(H).all()
+
+
 def train_inputs(rows, seed):
     rng = np.random.default_rng(seed)
     x = rng.normal(size=(rows, ccfmm.MLP_IN)).astype(np.float32)
