@@ -302,7 +302,11 @@ int ccfmm_plan_leaf_errors(ccfmm_plan plan, int32_t nbatch, const double* d_H, c
 /* Selector network (FP32, device arrays): forward pass of rows x [8] -> [25]. */
 int ccfmm_mlp_forward(const float* d_params, int64_t rows, const float* d_x, float* d_y, void* stream);
 /* Loss 0.5 sum mask (y - t)^2 / max(1, sum mask) and its gradient (d_grad
- * [CCFMM_MLP_PARAMS]); d_loss (1 float) may be NULL.  Deterministic. */
+ * [CCFMM_MLP_PARAMS]); d_loss (1 float) may be NULL.  Deterministic.
+ * May be captured after a call with as many rows on any stream (the library's
+ * partial sums are allocated then).  Graphs captured on up to four streams have
+ * partial sums of their own; replays of further ones, and of graphs captured on
+ * one stream, must not overlap. */
 int ccfmm_mlp_loss_grad(const float* d_params, int64_t rows, const float* d_x, const float* d_t,
                         const float* d_mask, float* d_grad, float* d_loss, void* stream);
 /* One Adam step (beta 0.9 / 0.999, bias-corrected; step counts from 1). */

@@ -1343,10 +1343,13 @@ int ccfmm_mlp_forward(const float* d_params, int64_t rows, const float* d_x, flo
 
 // Gradient partials of training steps, which have no handle to keep them: up
 // to four buffers per device, each bound to the stream that last used it.  A
-// call takes its stream's buffer, else one that no queued work uses any more,
-// else the next in turn, waiting on the stream for the work queued there, so
-// loops on several streams or threads do not share a buffer in use.  They are
-// never freed, so nothing touches the runtime during process teardown.
+// call takes its stream's buffer, else a new one, else the next in turn, waiting
+// on the stream for the work queued there, so loops on several streams or threads
+// do not share a buffer in use.  A buffer that a captured graph reads leaves them
+// and is neither grown nor handed to eager work any more (up to four more, one per
+// capturing stream; further captures share one that is large enough, and their
+// replays are kept apart by the caller).  They are never freed, so nothing touches
+// the runtime during process teardown.
 struct MlpScratch {
   DevBuf buf;
   hipStream_t st = nullptr;
@@ -1356,29 +1359,21 @@ struct MlpScratchPool {
   static constexpr int kSlots = 4, kDevices = 64;
   std::mutex mu;
   MlpScratch* slot[kDevices][kSlots] = {};
+  MlpScratch* graph[kDevices][kSlots] = {};
   int next[kDevices] = {};
   // (under mu) a buffer for work queued on st; none of its previous users'
   // work runs beside it
-  MlpScratch& take(int dev, hipStream_t st, bool capturing) {
-    MlpScratch* free_slot = nullptr;
+  MlpScratch& take(int dev, hipStream_t st) {
     int empty = -1;
     for (int i = 0; i < kSlots; i++) {
       MlpScratch* s = slot[dev][i];
       if (!s) {
         if (empty < 0) empty = i;
-        continue;
-      }
-      if (s->st == st) {  // (a destroyed stream's handle may have come back: wait all the same)
-        if (!capturing) CCFMM_HIP(hipStreamWaitEvent(st, s->done, 0));
+      } else if (s->st == st) {  // (a destroyed stream's handle may have come back: wait all the same)
+        CCFMM_HIP(hipStreamWaitEvent(st, s->done, 0));
         return *s;
       }
-      if (!free_slot && (capturing || hipEventQuery(s->done) == hipSuccess)) free_slot = s;
     }
-    (void)hipGetLastError();  // a pending event is no error
-    // a capture cannot allocate or wait for work outside it: it takes a buffer
-    // that is there, as its caller has to keep other training work apart from
-    // the replays anyway
-    if (free_slot && (capturing || empty < 0)) return *free_slot;
     if (empty >= 0) {
       MlpScratch* s = new MlpScratch();
       CCFMM_HIP(hipEventCreateWithFlags(&s->done, hipEventDisableTiming));
@@ -1388,6 +1383,36 @@ struct MlpScratchPool {
     MlpScratch* s = slot[dev][next[dev]++ % kSlots];
     CCFMM_HIP(hipStreamWaitEvent(st, s->done, 0));
     return *s;
+  }
+  // (under mu) a buffer of that size for a capture on st, which cannot wait for
+  // work outside it, nor in general allocate
+  MlpScratch& take_captured(int dev, hipStream_t st, size_t bytes) {
+    int empty = -1, shared = -1, own = -1;
+    for (int i = 0; i < kSlots; i++) {
+      MlpScratch* g = graph[dev][i];
+      if (!g) {
+        if (empty < 0) empty = i;
+      } else if (g->buf.cap >= bytes) {
+        if (g->st == st) return *g;
+        if (shared < 0) shared = i;
+      }
+      MlpScratch* s = slot[dev][i];
+      if (s && s->buf.cap >= bytes && (own < 0 || (s->st == st && slot[dev][own]->st != st))) own = i;
+    }
+    if (empty >= 0 && own >= 0) {
+      graph[dev][empty] = slot[dev][own];
+      slot[dev][own] = nullptr;
+      graph[dev][empty]->st = st;
+      return *graph[dev][empty];
+    }
+    if (shared >= 0) return *graph[dev][shared];
+    if (empty < 0) fail(CCFMM_ENOMEM, "no buffer of " + std::to_string(bytes) + " bytes for a captured training step");
+    // (a relaxed capture may allocate; others need a step of this size before them)
+    std::unique_ptr<MlpScratch> s(new MlpScratch());
+    s->buf.ensure(bytes);
+    s->st = st;
+    graph[dev][empty] = s.release();
+    return *graph[dev][empty];
   }
 };
 static MlpScratchPool& mlp_pool() {
@@ -1408,7 +1433,7 @@ int ccfmm_mlp_loss_grad(const float* d_params, int64_t rows, const float* d_x, c
     const bool capturing = cap != hipStreamCaptureStatusNone;
     MlpScratchPool& pool = mlp_pool();
     std::lock_guard<std::mutex> lk(pool.mu);
-    MlpScratch& s = pool.take(dev, st, capturing);
+    MlpScratch& s = capturing ? pool.take_captured(dev, st, mlp_grad_bytes(rows)) : pool.take(dev, st);
     run_mlp_loss_grad(d_params, rows, d_x, d_t, d_mask, d_grad, d_loss, s.buf, st);
     if (!capturing) {
       s.st = st;

@@ -284,6 +284,7 @@ void run_leaf_errors(Plan& P, int nb, const double* d_H, const double* d_Href, d
                      hipStream_t st);
 void run_leaf_features(Plan& P, int nb, const double* d_m, float* d_feat, hipStream_t st);
 void run_mlp_forward(const float* d_params, int64_t rows, const float* d_x, float* d_y, hipStream_t st);
+size_t mlp_grad_bytes(int64_t rows);  // of tmp
 void run_mlp_loss_grad(const float* d_params, int64_t rows, const float* d_x, const float* d_t, const float* d_mask,
                        float* d_grad, float* d_loss, DevBuf& tmp, hipStream_t st);
 void run_mlp_adam(float* d_params, const float* d_grad, float* d_m1, float* d_m2, int step, float lr,

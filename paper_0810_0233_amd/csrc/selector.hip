@@ -572,10 +572,14 @@ void run_mlp_forward(const float* d_params, int64_t rows, const float* d_x, floa
   CCFMM_HIP(hipGetLastError());
 }
 
+size_t mlp_grad_bytes(int64_t rows) {
+  return (sizeof(GradShare) + sizeof(float) * kParams) * (size_t)std::max(1, ceil_div(rows, kGR));
+}
+
 void run_mlp_loss_grad(const float* d_params, int64_t rows, const float* d_x, const float* d_t, const float* d_mask,
                        float* d_grad, float* d_loss, DevBuf& tmp, hipStream_t st) {
   const int nblk = std::max(1, ceil_div(rows, kGR));
-  char* buf = reinterpret_cast<char*>(tmp.ensure(sizeof(GradShare) * nblk + sizeof(float) * (size_t)nblk * kParams));
+  char* buf = reinterpret_cast<char*>(tmp.ensure(mlp_grad_bytes(rows)));
   GradShare* share = reinterpret_cast<GradShare*>(buf);
   float* part = reinterpret_cast<float*>(share + nblk);
   k_mlp_grad_part<<<nblk, 256, 0, st>>>(d_params, rows, d_x, d_t, d_mask, part, share);

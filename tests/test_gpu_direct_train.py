@@ -130,3 +130,42 @@ def test_training_loops_on_several_streams():
         torch.cuda.synchronize()
         for g, a in zip(grads, alone):
             assert torch.equal(g, a)
+
+
+def test_captured_step_keeps_its_buffer():
+    """A step captured on a third stream, after smaller and equal ones on two others,
+    gives the eager gradient on every replay, with larger eager steps between."""
+    import torch
+
+    def step(s, rows, g, st):
+        ccfmm.mlp_loss_grad(s[3].data_ptr(), rows, s[0].data_ptr(), s[1].data_ptr(), s[2].data_ptr(), g.data_ptr(), None,
+                            st.cuda_stream)
+
+    sets = {r: [torch.from_numpy(v).cuda() for v in train_inputs(r, r)] for r in (64, 5000, 9000)}
+    grads = {r: torch.empty_like(sets[r][3]) for r in sets}
+    a, b, c, d, e = (torch.cuda.Stream() for _ in range(5))
+    torch.cuda.synchronize()
+    step(sets[64], 64, grads[64], a)
+    step(sets[5000], 5000, grads[5000], b)
+    torch.cuda.synchronize()
+    want = grads[5000].clone()
+    torch.cuda.synchronize()
+    graphs = []
+    for st in (c, d):
+        g, out = torch.cuda.CUDAGraph(), torch.empty_like(want)
+        with torch.cuda.graph(g, stream=st):
+            step(sets[5000], 5000, out, st)
+        graphs.append((g, out))
+        torch.cuda.synchronize()
+        step(sets[5000], 5000, grads[5000], e)  # (a buffer for the next capture)
+        torch.cuda.synchronize()
+    for rep in range(4):
+        for st in (a, b, c, d, e):
+            step(sets[9000], 9000, grads[9000], st)
+            torch.cuda.synchronize()
+        for g, out in graphs:
+            out.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            print("case replay %d" % rep, flush=True)
+            assert torch.equal(out, want)
