@@ -858,8 +858,8 @@ int ccfmm_eval_device_timed(ccfmm_plan plan, int32_t nbatch, const double* d_m, 
     prepare_batch(P, nbatch, st);
     hipEvent_t ev[9];
     create_pass_events(ev, 9, 5);
-    // every pass alone on the caller's stream (the near field fused with L2P
-    // below the batched size), so each time is that pass's own cost
+    // every pass alone on the caller's stream (near field and L2P timed together
+    // except after the FP16 near field), so each time is that pass's own cost
     const bool overlap = P.overlap;
     P.overlap = false;
     try {

@@ -1,5 +1,5 @@
-// mfma.hpp -- the 16x16x4 matrix-core instructions used by the M2L and batched
-// near-field kernels, and their register layouts on gfx950.
+// mfma.hpp -- the 16x16x4 matrix-core instructions of the M2L kernels, and their
+// register layouts on gfx950.
 //
 // Operands: lane l supplies A[row l%16][k l/16] and B[k l/16][column l%16].
 // Result: lane l holds column l%16; its item r is row 4 (l/16) + r for FP32

@@ -13,8 +13,9 @@ __device__ __forceinline__ float rsqrt_t<float>(float x) {
 template <>
 __device__ __forceinline__ double rsqrt_t<double>(double x) {
   // hardware estimate y (relative error e/2 below 2^-22, e = 1 - x y^2)
-  // refined by one third-order step y (1 + e/2 + 3 e^2/8): five operations
-  // where two Newton steps take eight, and the cubed error is far below 2^-53
+  // refined by one third-order step y (1 + e/2 + 3 e^2/8), the binomial series
+  // of (1 - e)^(-1/2): five operations where two Newton steps take eight, and the
+  // cubed error is far below 2^-53.  (x beyond FP64's range gives inf 0, not zero.)
   const double y = __builtin_amdgcn_rsq(x);
   const double e = fma(-(x * y), y, 1.0);
   return fma(y * e, fma(0.375, e, 0.5), y);

@@ -17,7 +17,6 @@
 #include <mutex>
 #include <type_traits>
 
-#include "mfma.hpp"
 #include "near.hpp"
 
 namespace ccfmm {
@@ -150,42 +149,53 @@ __device__ __forceinline__ void p2p_role(const P2PSrc<T>* __restrict__ src, cons
   }
 }
 
+// ------------------------------------------------------------ smooth field
+// Gradient of the local expansion of a dipole's cell, degree by degree up to the
+// cell's order, from the monomials y^k / k! (factors px, py, pz).
+template <typename T, int P>
+struct SmoothMono {
+  T px[P], py[P], pz[P];
+  __device__ __forceinline__ SmoothMono(T yx, T yy, T yz) {
+    px[0] = py[0] = pz[0] = (T)1;
+#pragma unroll
+    for (int j = 1; j < P; j++) {
+      const T inv = (T)(1.0 / j);
+      px[j] = px[j - 1] * yx * inv;
+      py[j] = py[j - 1] * yy * inv;
+      pz[j] = pz[j - 1] * yz * inv;
+    }
+  }
+  __device__ __forceinline__ void gradient(const T* __restrict__ v, int pl, T (&e)[3]) const {
+    e[0] = e[1] = e[2] = (T)0;
+#pragma unroll
+    for (int d = 0; d < P; d++) {
+      if (d >= pl) break;
+#pragma unroll
+      for (int k = ncoef(d - 1); k < ncoef(d); k++) {
+        const int kx = kMI.x[k], ky = kMI.y[k], kz = kMI.z[k];
+        const T mono = px[kx] * py[ky] * pz[kz];
+        e[0] += v[midx(kx + 1, ky, kz) - 1] * mono;
+        e[1] += v[midx(kx, ky + 1, kz) - 1] * mono;
+        e[2] += v[midx(kx, ky, kz + 1) - 1] * mono;
+      }
+    }
+  }
+};
+
 // Smooth field of one dipole from its cell's local expansion,
 // H_a = -sum_{|k| <= pl-1} Vt_{k+e_a} yt^k / k!, plus the near field.
 template <typename T, int P>
 __device__ __forceinline__ void l2p_write(const T* __restrict__ v, int pl, T yx, T yy, T yz, double hx, double hy,
                                           double hz, double s3, double* __restrict__ Ho) {
-  constexpr int NM = ncoef(P - 1);
-  T px[P], py[P], pz[P];
-  px[0] = py[0] = pz[0] = (T)1;
-#pragma unroll
-  for (int j = 1; j < P; j++) {
-    const T inv = (T)(1.0 / j);
-    px[j] = px[j - 1] * yx * inv;
-    py[j] = py[j - 1] * yy * inv;
-    pz[j] = pz[j - 1] * yz * inv;
-  }
-  (void)NM;
-  T ex = (T)0, ey = (T)0, ez = (T)0;
-  // degree by degree (the monomials are ordered by degree): a smallest cell
-  // with its own order pl keeps |n| <= pl, i.e. |k| <= pl - 1, and stops there
-#pragma unroll
-  for (int d = 0; d < P; d++) {
-    if (d >= pl) break;
-#pragma unroll
-    for (int k = ncoef(d - 1); k < ncoef(d); k++) {
-      const int kx = kMI.x[k], ky = kMI.y[k], kz = kMI.z[k];
-      const T mono = px[kx] * py[ky] * pz[kz];
-      ex += v[midx(kx + 1, ky, kz) - 1] * mono;
-      ey += v[midx(kx, ky + 1, kz) - 1] * mono;
-      ez += v[midx(kx, ky, kz + 1) - 1] * mono;
-    }
-  }
-  Ho[0] = s3 * (hx - (double)ex);
-  Ho[1] = s3 * (hy - (double)ey);
-  Ho[2] = s3 * (hz - (double)ez);
+  const SmoothMono<T, P> mono(yx, yy, yz);
+  T e[3];
+  mono.gradient(v, pl, e);
+  Ho[0] = s3 * (hx - (double)e[0]);
+  Ho[1] = s3 * (hy - (double)e[1]);
+  Ho[2] = s3 * (hz - (double)e[2]);
 }
 
+// ------------------------------------------------------------ one configuration
 // The near field of one configuration alone (written, not added): the smooth
 // field is added by k_l2p_one.  kSplit: the wavefronts of a block share
 // chunks (near_split).
@@ -426,8 +436,9 @@ __global__ void __launch_bounds__(64 * kP2PWaves, sizeof(T) == 4 ? 6 : 2) k_p2p_
 }
 
 // ------------------------------------------------------------ a few configurations
-// Near field for 2..31 configurations on the vector units.  The geometry of a
-// pair -- separation, reciprocal distance, r^-2 and r^-3 -- is the same for
+// Near field of several configurations on the vector units: FP64 plans, and in
+// mixed ones two configurations of large plans, plans without room for the FP16
+// form and configurations that it leaves (P2PArgs::range).  The geometry of a pair -- separation, reciprocal distance, r^-2 and r^-3 -- is the same for
 // every configuration, so it is formed once and applied to KB configurations
 // held by the same lane: about 13 + 10 KB operations per pair instead of
 // 23 KB (in FP64 about 24 + 9 KB; vector and matrix-core FP64 run at the same
@@ -805,38 +816,6 @@ __global__ void __launch_bounds__(64 * kP2PWaves, (multi_waves<T, KB, PL>())) k_
 }
 
 // ------------------------------------------------------------ smooth field
-// Gradient of the local expansion of a dipole's cell, degree by degree up to the
-// cell's order, from the monomials y^k / k! (factors px, py, pz).
-template <typename T, int P>
-struct SmoothMono {
-  T px[P], py[P], pz[P];
-  __device__ __forceinline__ SmoothMono(T yx, T yy, T yz) {
-    px[0] = py[0] = pz[0] = (T)1;
-#pragma unroll
-    for (int j = 1; j < P; j++) {
-      const T inv = (T)(1.0 / j);
-      px[j] = px[j - 1] * yx * inv;
-      py[j] = py[j - 1] * yy * inv;
-      pz[j] = pz[j - 1] * yz * inv;
-    }
-  }
-  __device__ __forceinline__ void gradient(const T* __restrict__ v, int pl, T (&e)[3]) const {
-    e[0] = e[1] = e[2] = (T)0;
-#pragma unroll
-    for (int d = 0; d < P; d++) {
-      if (d >= pl) break;
-#pragma unroll
-      for (int k = ncoef(d - 1); k < ncoef(d); k++) {
-        const int kx = kMI.x[k], ky = kMI.y[k], kz = kMI.z[k];
-        const T mono = px[kx] * py[ky] * pz[kz];
-        e[0] += v[midx(kx + 1, ky, kz) - 1] * mono;
-        e[1] += v[midx(kx, ky + 1, kz) - 1] * mono;
-        e[2] += v[midx(kx, ky, kz + 1) - 1] * mono;
-      }
-    }
-  }
-};
-
 // The smooth field added to the near field in H (FP64, caller order): one
 // configuration, one thread per dipole.
 template <typename T, int P>
@@ -1310,8 +1289,11 @@ void run_energy_noalloc(int64_t n, int nb, const double* d_m, const double* d_H,
 void run_direct_targets(int64_t n, const double* d_pos, const double* d_m, int64_t nt, const int64_t* d_idx,
                         double* d_H, hipStream_t st) {
   if (nt <= 0) return;
-  // targets per block: as many as leave a block for every compute unit (the
-  // sources are read once per block)
+  // Targets per block (the sources are read once for them): one while those blocks
+  // fill the compute units once, then two, then four, which beat fewer also where
+  // their blocks leave units idle (2^20 dipoles, one, two and four a block: 256
+  // targets 597, 617 and 1,067 us, 300 1,047, 604 and 1,064, 600 1,550, 1,219 and
+  // 1,067, 1,024 2,095, 1,375 and 1,210).
   if (nt > 512)
     k_direct_targets<4><<<ceil_div(nt, 4), kDirectThreads, 0, st>>>(n, d_pos, d_m, nt, d_idx, d_H);
   else if (nt > 256)
