@@ -58,7 +58,8 @@ typedef struct {
                            s_o = 0.74 p^2 for p > 3, else 8 */
   int32_t leaf_rule;    /* 0: levels L = argmin_L |N/2^L - s| (Sec. 4);
                            1: same with N/2^L replaced by the mean over occupied cells */
-  int32_t precision;    /* CCFMM_PREC_FP64 or CCFMM_PREC_MIXED */
+  int32_t precision;    /* CCFMM_PREC_FP64 or CCFMM_PREC_MIXED (FP32 accuracy; moments of
+                           1e-35 to 1e34 in magnitude, zeros included) */
   int32_t selector;     /* 0: fixed (order, theta) everywhere.  1: learned per smallest cell:
                            once the plan holds selector weights (ccfmm_selector_load / _set),
                            the first evaluation after the plan is built, or after a position
@@ -114,7 +115,11 @@ typedef struct {
   int64_t device_mem_cap; /* bytes of device memory the plan may hold (its buffers and the
                              temporaries of its calls); 0 (default): no cap.  A call that would
                              pass it fails with CCFMM_ENOMEM; the plan stays destroyable, and
-                             after a failed evaluation it evaluates again at sizes that fit */
+                             after a failed evaluation it evaluates again at sizes that fit.
+                             The FP16 near field's buffers and the sums of cut M2L step lists
+                             are held only where there is room beside the rest.  When the device
+                             itself has no memory left, a plan also goes on without them and
+                             with the smaller FP32 M2L operators */
 } ccfmm_params;
 
 /* One timed M2L configuration of ccfmm_plan_autotune. */
